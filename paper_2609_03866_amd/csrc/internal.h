@@ -506,6 +506,7 @@ __host__ __device__ constexpr int reg_grids(int mode) {
 // the grid is written once and read once.
 constexpr int kRegTile = 2048;   // positions per tile of the fused route (its last radix)
 constexpr int kRegSegCells = 8;  // lattice cells per entry of the sample-index table
+constexpr int64_t kRegFusedMax = 1 << 20;  // largest transform of the fused route
 // Limits of the fused route, all of them of capacity: the first pass needs
 // whole table entries per row of its 4096-cell tiles (N <= 2^20), the lags one
 // entry per tile position (Q < kRegTile), and the table lies in the room of the
@@ -514,7 +515,7 @@ constexpr int kRegSegCells = 8;  // lattice cells per entry of the sample-index 
 // samples on N = 2^20 150, 112 us; 256 series of 1252 samples on 20,000 cells
 // 358, 223 us) or ties (100,000 samples, Q = 2047: 129, 131 us).
 __host__ __device__ constexpr bool reg_fused(int64_t n, int64_t G, int64_t Q, int64_t N) {
-    return N <= (1 << 20) && Q < kRegTile && n >= G / 16 + 2;
+    return N <= kRegFusedMax && Q < kRegTile && n >= G / 16 + 2;
 }
 
 struct RegTask {

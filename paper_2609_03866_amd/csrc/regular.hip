@@ -152,9 +152,18 @@ __device__ __forceinline__ double reg_lat(double tv, double t_ref, double inv_dt
 
 // Sample-index table of one chunk of one task: sample i is the first at or
 // past the cells 8b that lie in (index of sample i - 1, index of sample i].
-// One coalesced pass over the times.
+// One coalesced pass over the times. The entries of a gap between two samples
+// are written by the sample's lane up to 32 of them, by its wave up to
+// kSegWide, and by the workgroup after its pass beyond (two campaigns 975,000
+// cells apart, 66,000 samples: one lane 3,160 us the call, this 112).
+constexpr int kSegWide = 4096;
+
 __global__ void __launch_bounds__(kThreads)
 k_reg_seg(const RegTask* __restrict__ tasks, const int64_t* __restrict__ blk0, int ntasks) {
+    // gaps of more than kSegWide entries in one table of a fused problem
+    constexpr int kGaps = kRegFusedMax / kRegSegCells / kSegWide;
+    __shared__ int32_t gap[kGaps][3];  // first entry, last entry, sample
+    __shared__ int32_t ngap;
     const int64_t b = blockIdx.x;
     const int ti = ntasks == 1 ? 0 : (int)wave_search<int64_t>(blk0, ntasks, b, true) - 1;
     const RegTask& T = tasks[ti];
@@ -165,15 +174,40 @@ k_reg_seg(const RegTask* __restrict__ tasks, const int64_t* __restrict__ blk0, i
     const gptr<int32_t> seg = gbl(T.seg);
     const double inv_dt = 1.0 / T.dt, top = (double)(T.G - 1);
     auto block_of = [&](double tv) {
-        return (int64_t)fmin(fmax(reg_lat(tv, T.t_ref, inv_dt), 0.0), top) / kRegSegCells;
+        return (int32_t)((int64_t)fmin(fmax(reg_lat(tv, T.t_ref, inv_dt), 0.0), top) /
+                         kRegSegCells);
     };
-    const int64_t nseg = (T.G + kRegSegCells - 1) / kRegSegCells;
-    for (int64_t i = i0 + threadIdx.x; i < i1; i += kThreads) {
-        const int64_t e = block_of(t[i]);
-        for (int64_t q = i > 0 ? block_of(t[i - 1]) + 1 : 0; q <= e; ++q) seg[q] = (int32_t)i;
-        if (i == n - 1)
-            for (int64_t q = e + 1; q <= nseg; ++q) seg[q] = (int32_t)n;
+    const int32_t nseg = (int32_t)((T.G + kRegSegCells - 1) / kRegSegCells);
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (tid == 0) ngap = 0;
+    __syncthreads();
+    for (int64_t r = i0; r < i1; r += kThreads) {
+        const int64_t i = r + tid;
+        const bool live = i < i1;
+        const int32_t e = live ? block_of(t[i]) : -1;
+        const int32_t p = live && i > 0 ? block_of(t[i - 1]) : -1;
+        const bool wide = live && e - p > 32;
+        if (live && !wide)
+            for (int32_t q = p + 1; q <= e; ++q) seg[q] = (int32_t)i;
+        for (uint64_t m = __ballot(wide); m; m &= m - 1) {
+            const int l = __ffsll((unsigned long long)m) - 1;
+            const int32_t q0 = __shfl(p, l) + 1, q1 = __shfl(e, l);
+            const int32_t v = (int32_t)(r + (tid & ~63) + l);
+            if (q1 - q0 < kSegWide) {
+                for (int32_t q = q0 + lane; q <= q1; q += 64) seg[q] = v;
+            } else if (lane == 0) {
+                const int k = atomicAdd(&ngap, 1);
+                gap[k][0] = q0;
+                gap[k][1] = q1;
+                gap[k][2] = v;
+            }
+        }
+        if (live && i == n - 1)
+            for (int32_t q = e + 1; q <= nseg; ++q) seg[q] = (int32_t)n;
     }
+    __syncthreads();
+    for (int k = 0; k < ngap; ++k)
+        for (int32_t q = gap[k][0] + tid; q <= gap[k][1]; q += kThreads) seg[q] = gap[k][2];
 }
 
 // First transform pass of the fused route: a tile is 2^LGR rows (cells
