@@ -507,15 +507,21 @@ __host__ __device__ constexpr int reg_grids(int mode) {
 constexpr int kRegTile = 2048;   // positions per tile of the fused route (its last radix)
 constexpr int kRegSegCells = 8;  // lattice cells per entry of the sample-index table
 constexpr int64_t kRegFusedMax = 1 << 20;  // largest transform of the fused route
-// Limits of the fused route, all of them of capacity: the first pass needs
-// whole table entries per row of its 4096-cell tiles (N <= 2^20), the lags one
-// entry per tile position (Q < kRegTile), and the table lies in the room of the
-// n standardized values, which this route does not store. Up to them it is
-// the faster one (general, fused; 1000 samples and 100 lags 85, 82 us; 500,000
+// Limits of the fused route. Three are of capacity: the first pass needs whole
+// table entries per row of its 4096-cell tiles (N <= 2^20), the lags one entry
+// per tile position (Q < kRegTile), and the table lies in the room of the n
+// standardized values, which this route does not store. Up to them it is the
+// faster one (general, fused; 1000 samples and 100 lags 85, 82 us; 500,000
 // samples on N = 2^20 150, 112 us; 256 series of 1252 samples on 20,000 cells
-// 358, 223 us) or ties (100,000 samples, Q = 2047: 129, 131 us).
+// 358, 223 us) or ties (100,000 samples, Q = 2047: 129, 131 us). The fourth is
+// of repeated times: one workgroup gathers 4096 cells there, 1024 in the general
+// fill, and runs of samples in one cell are summed by one lane (60,000 cells,
+// general and fused: 3 samples per cell 119, 120 us, 4 136, 138, 6 156, 191, 16
+// 376, 754); a transform of one tile is the faster one fused at any count
+// (500 cells, 64 per cell 1371, 1251 us).
 __host__ __device__ constexpr bool reg_fused(int64_t n, int64_t G, int64_t Q, int64_t N) {
-    return N <= kRegFusedMax && Q < kRegTile && n >= G / 16 + 2;
+    return N <= kRegFusedMax && Q < kRegTile && n >= G / 16 + 2 &&
+           (n <= 4 * G || N == 2 * kRegTile);
 }
 
 struct RegTask {
