@@ -1879,8 +1879,7 @@ void CallRun::plan_window(WinLaunch& W) {
     // waves per SIMD; the Gaussian scan has registers for six, 24 KB (2048
     // rectangle pairs: 24 KB 21.4 ms, 18 KB 19.4; 10,000 weighted series: 64.0,
     // 65.9 ms)
-    const int budget = (rect ? 18 : 24) * 1024 / 8;
-    int cap = budget / arrays - 8;
+    int cap = (rect ? 18 * 1024 / 8 / arrays : gauss_entry(arrays)) - 8;
     cap = std::max(256, std::min(4096, cap));
     const int ntask = (int)W.plans.size();
     W.wt.assign(ntask, WinTask{});

@@ -170,34 +170,38 @@ struct AccG {
     N points;
 };
 
-// Gaussian window samples staged in LDS as records of S doubles (time, then
-// value and weight where the launch sums them), followed by +inf times; a
-// window bound is a record address.
+// Gaussian window samples staged in LDS: the times, followed by +inf, and the
+// S - 1 arrays that the launch sums beside them (values, weights) at multiples
+// of kEntry doubles, so that one address and constant offsets reach a sample's
+// entries; a window bound is the address of a time. Arrays, not records of S
+// doubles: lanes that are several samples apart read records with bank
+// conflicts (100,000 samples, 16 per day, 256 lags 0.5 days apart, FP32 scan,
+// the call: values alone 2.64 ms as records, 1.37 so; with weights 2.23, 1.58).
 template <int S>
 struct GaussLds {
+    static constexpr int kEntry = gauss_entry(S);
     typedef const double* P;
-    typedef int N;  // at most 1024 outer samples of 4096 points each, times 24 bytes
-    __device__ __forceinline__ double T(P p, int i = 0) const { return p[S * i]; }
-    __device__ __forceinline__ double A(P p, int q) const { return p[q]; }
-    __device__ __forceinline__ P next(P p) const { return p + S; }
-    __device__ __forceinline__ P move(P p, int n) const {
-        return (P)((const char*)p + __umul24(n, 8 * S));
-    }
-    __device__ __forceinline__ int dist(P a, P b) const {  // in units of 8 S bytes, times 8 S
+    typedef int N;  // at most 1024 outer samples of 4096 points each, times 8 bytes
+    __device__ __forceinline__ double T(P p, int i = 0) const { return p[i]; }
+    __device__ __forceinline__ double A(P p, int q, int i = 0) const { return p[kEntry * q + i]; }
+    __device__ __forceinline__ P move(P p, int n) const { return p + n; }
+    static constexpr int kUnit = 8;
+    __device__ __forceinline__ int dist(P a, P b) const {  // samples from a to b, times kUnit
         return (int)((const char*)b - (const char*)a);
     }
-    static constexpr int kUnit = 8 * S;
-    // first record at or after `base` (of len) whose time is >= key
+    // doubles that hold `cap` samples and their sentinels
+    static constexpr size_t size(int cap) { return (size_t)kEntry * (S - 1) + cap + 8; }
+    // first of the len staged times that is >= key
     __device__ __forceinline__ P lower(int len, double key) const {
         int lo = 0, hi = len;
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
-            if (g_win_lds[S * mid] < key)
+            if (g_win_lds[mid] < key)
                 lo = mid + 1;
             else
                 hi = mid;
         }
-        return g_win_lds + S * lo;
+        return g_win_lds + lo;
     }
 };
 
@@ -213,10 +217,9 @@ struct GaussGlb {
         const double v = t[min(p + i, len - 1)];
         return p + i < len ? v : kInf;
     }
-    __device__ __forceinline__ double A(P p, int q) const {
-        return (q == 1 ? a1 : a2)[min(p, len - 1)];
+    __device__ __forceinline__ double A(P p, int q, int i = 0) const {
+        return (q == 1 ? a1 : a2)[min(p + i, len - 1)];
     }
-    __device__ __forceinline__ P next(P p) const { return p + 1; }
     __device__ __forceinline__ P move(P p, int n) const { return p + n; }
     __device__ __forceinline__ int dist(P a, P b) const { return b - a; }
     __device__ __forceinline__ P lower(int n, double key) const {
@@ -236,9 +239,9 @@ struct GaussGlb {
 // per round), then add the weights of the samples up to the first time at or
 // past the window's end (so the scan keeps no upper bound). The next point's
 // record is read before the current weight is formed. Bound by issue: a weight
-// is 12 instructions of FP64 rate, the FP32 exponential and its scaling. Records
-// (one address for time, value and weight), no second bound, unstaged outer
-// samples (24 KB of LDS instead of 40, more waves to cover the chain): 10,000
+// is 12 instructions of FP64 rate, the FP32 exponential and its scaling. One
+// address for time, value and weight, no second bound, unstaged outer samples
+// (24 KB of LDS instead of 40, more waves to cover the chain): 10,000
 // weighted series, 5.8e10 weights, 94.3 -> 70.8 ms the call. Reading the
 // exponent off the bits of the floor instead of a conversion and ldexp: 79 ms.
 template <uint32_t F, typename V>
@@ -260,25 +263,27 @@ __device__ __forceinline__ void gauss_step(AccG<typename V::N>& acc, const V& v,
         if (a < kAdv) break;
     }
     typename V::P i = lo;
-    double t = v.T(i), a1 = NUMER ? v.A(i, 1) : 0.0, a2 = WTD ? v.A(i, QW) : 0.0;
     double bj = 0.0, Cj = 0.0, Bj = 0.0;
-    while (t < hk) {
-        const double d = t - c;  // FP64 difference
-        const double b1 = a1, b2 = a2;
-        i = v.next(i);
-        t = v.T(i);
-        if (NUMER) a1 = v.A(i, 1);
-        if (WTD) a2 = v.A(i, QW);
-        double e;
-        if (E64) {
-            const double z = d * inv_h;
-            e = exp(-0.5 * z * z);
-        } else {
-            e = gauss_w32(d, k2);
+    {
+        double t = v.T(i), a1 = NUMER ? v.A(i, 1) : 0.0, a2 = WTD ? v.A(i, QW) : 0.0;
+        while (t < hk) {
+            const double d = t - c;  // FP64 difference
+            const double b1 = a1, b2 = a2;
+            i = v.move(i, 1);
+            t = v.T(i);
+            if (NUMER) a1 = v.A(i, 1);
+            if (WTD) a2 = v.A(i, QW);
+            double e;
+            if (E64) {
+                const double z = d * inv_h;
+                e = exp(-0.5 * z * z);
+            } else {
+                e = gauss_w32(d, k2);
+            }
+            bj += e;  // FP64 sums: windows of bursty samples hold thousands of points
+            if (NUMER) Cj += e * b1;
+            if (WTD) Bj += e * b2;
         }
-        bj += e;  // FP64 sums: windows of bursty samples hold thousands of points
-        if (NUMER) Cj += e * b1;
-        if (WTD) Bj += e * b2;
     }
     acc.points += v.dist(lo, i);
     acc.b += bj;
@@ -545,8 +550,8 @@ __device__ __forceinline__ void window_item(const WinTask* __restrict__ tasks,
     const double* A2g = RECT ? T.pw : T.w;
     // rectangle: times, then the prefix arrays (each cap + 8 long: values,
     // weights and the nonzero-weight count), or with values only (no
-    // weights) each time paired with its value prefix. Gaussian: records of
-    // (time, value, weight), those the launch sums. The outer samples stay
+    // weights) each time paired with its value prefix. Gaussian: times, values
+    // and weights, those the launch sums (GaussLds). The outer samples stay
     // in global memory
     constexpr int QW = NUMER ? 2 : 1;
     const int dp = cap + 8;
@@ -601,12 +606,13 @@ __device__ __forceinline__ void window_item(const WinTask* __restrict__ tasks,
                 }
             }
         } else if (fits) {
+            constexpr int E = GaussLds<GS>::kEntry;
             for (int i = tid; i < len + 8; i += kThreads) {
-                double* r = g_win_lds + GS * i;
+                double* r = g_win_lds + i;
                 const bool in = i < len;
                 r[0] = in ? gt[tlo + i] : kInf;
-                if (NUMER) r[1] = in ? ga1[tlo + i] : 0.0;
-                if (WTD) r[GS - 1] = in ? ga2[tlo + i] : 0.0;
+                if (NUMER) r[E] = in ? ga1[tlo + i] : 0.0;
+                if (WTD) r[E * (GS - 1)] = in ? ga2[tlo + i] : 0.0;
             }
         }
         __syncthreads();
@@ -944,7 +950,13 @@ int launch_window_t(const WinTask* d_tasks, const int64_t* d_item0, int ntasks, 
     constexpr bool RECT = (F & WIN_RECT) != 0;
     constexpr bool NUMER = (F & WIN_NUMER) != 0;
     constexpr bool WTD = (F & WIN_WEIGHTED) != 0;
-    size_t stage = (size_t)(cap + 8) * (1 + (NUMER ? 1 : 0) + (WTD ? (RECT ? 2 : 1) : 0));
+    constexpr int GS = 1 + (NUMER ? 1 : 0) + (WTD ? 1 : 0);
+    if (!RECT && cap + 8 > GaussLds<GS>::kEntry) {
+        set_error("window scan: room for %d of %d staged samples", GaussLds<GS>::kEntry - 8, cap);
+        return NCF_E_UNSUPPORTED;
+    }
+    size_t stage = RECT ? (size_t)(cap + 8) * (1 + (NUMER ? 1 : 0) + (WTD ? 2 : 0))
+                        : GaussLds<GS>::size(cap);
     size_t red = 4 * kThreads;
     size_t bytes = (stage > red ? stage : red) * sizeof(double);
     (void)RECT;
