@@ -315,13 +315,11 @@ int launch_window_reduce(const WinTask* d_tasks, int ntasks, int64_t total_k, co
                          const int64_t* d_r0, int64_t nred1, int64_t few, uint32_t flags,
                          hipStream_t st);  // few: lag tiles of a one-launch reduction, or 0
 // A Gaussian window scan stages its window range in 24 KB of LDS: S arrays
-// (times, values, weights), gauss_entry(S) doubles apart. Three are no multiple
+// (times, values, weights), gauss_entry(S) doubles apart. They are no multiple
 // of 512 bytes apart: two reads at such a distance become one instruction,
 // whose halves meet in the same banks (100,000 weighted samples, 16 per day, 256
 // lags 0.5 days apart, the call: 2.27 ms so, 1.58).
-__host__ __device__ constexpr int gauss_entry(int S) {
-    return 24 * 1024 / 8 / S - (S == 3 ? 2 : 0);
-}
+__host__ __device__ constexpr int gauss_entry(int S) { return 24 * 1024 / 8 / S - (S > 1 ? 2 : 0); }
 constexpr int kWinJc = 64;          // j-groups per first-level reduction block
 constexpr int kWinGroupMax = 16;    // most j-tiles per window work item
 constexpr int kWinItemsFew = 1024;   // items that a launch should have (see plan_window)

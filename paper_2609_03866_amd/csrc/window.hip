@@ -180,6 +180,7 @@ struct AccG {
 template <int S>
 struct GaussLds {
     static constexpr int kEntry = gauss_entry(S);
+    static constexpr bool kGlobal = false;
     typedef const double* P;
     typedef int N;  // at most 1024 outer samples of 4096 points each, times 8 bytes
     __device__ __forceinline__ double T(P p, int i = 0) const { return p[i]; }
@@ -208,6 +209,7 @@ struct GaussLds {
 // The same samples in global memory (a range that does not fit in LDS); a
 // window bound is an index. a1, a2: the arrays of the record entries 1 and 2.
 struct GaussGlb {
+    static constexpr bool kGlobal = true;
     typedef int P;
     typedef int64_t N;
     gdp t, a1, a2;
@@ -236,18 +238,24 @@ struct GaussGlb {
 };
 
 // One outer sample of the Gaussian scan: move `lo` to its window (kAdv reads
-// per round), then add the weights of the samples up to the first time at or
-// past the window's end (so the scan keeps no upper bound). The next point's
-// record is read before the current weight is formed. Bound by issue: a weight
-// is 12 instructions of FP64 rate, the FP32 exponential and its scaling. One
-// address for time, value and weight, no second bound, unstaged outer samples
-// (24 KB of LDS instead of 40, more waves to cover the chain): 10,000
+// per round), then add the weights of its samples. Bound by issue: an FP32 weight
+// is 12 instructions of FP64 rate, the exponential and its scaling. One address
+// for time, value and weight, unstaged outer samples (24 KB of LDS instead of
+// 40, more waves to cover the chain) and, with the FP32 exponential, no upper
+// bound, the next sample read before the current weight is formed: 10,000
 // weighted series, 5.8e10 weights, 94.3 -> 70.8 ms the call. Reading the
 // exponent off the bits of the floor instead of a conversion and ldexp: 79 ms.
+// The FP64 exponential (40 instructions in a chain) takes the samples up to an
+// upper bound `hi` by twos: 500 series of 2000 samples, 12 samples per window,
+// the call: to the first time past the window one by one 2.97 ms, by fours 3.06;
+// to the bound one by one 3.00, by twos 2.73, by fours 2.81. On samples in global
+// memory, to the first time past the window by fours: their loads are in flight
+// together (100,000 weighted samples, 288 per window: one by one 27.1 ms, to the
+// bound by fours 28.5, so 21.9).
 template <uint32_t F, typename V>
-__device__ __forceinline__ void gauss_step(AccG<typename V::N>& acc, const V& v, typename V::P& lo, double s,
-                                           double vo, double wo, double delta, double W,
-                                           double inv_h, double k2) {
+__device__ __forceinline__ void gauss_step(AccG<typename V::N>& acc, const V& v, typename V::P& lo,
+                                           typename V::P& hi, double s, double vo, double wo,
+                                           double delta, double W, double inv_h, double k2) {
     constexpr bool NUMER = (F & WIN_NUMER) != 0;
     constexpr bool WTD = (F & WIN_WEIGHTED) != 0;
     constexpr bool E64 = (F & WIN_EXP64) != 0;
@@ -264,7 +272,49 @@ __device__ __forceinline__ void gauss_step(AccG<typename V::N>& acc, const V& v,
     }
     typename V::P i = lo;
     double bj = 0.0, Cj = 0.0, Bj = 0.0;
-    {
+    auto weigh = [&](double d, int m) {
+        const double z = d * inv_h;
+        const double e = exp(-0.5 * z * z);
+        bj += e;
+        if (NUMER) Cj += e * v.A(i, 1, m);
+        if (WTD) Bj += e * v.A(i, QW, m);
+    };
+    if constexpr (E64 && V::kGlobal) {
+        for (;;) {
+            double t[4];
+            int a = 0;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                t[m] = v.T(i, m);
+                a += t[m] < hk;
+            }
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                if (m < a) weigh(t[m] - c, m);
+            i = v.move(i, a);
+            if (a < 4) break;
+        }
+    } else if constexpr (E64) {
+        for (;;) {
+            int a = 0;
+#pragma unroll
+            for (int q = 0; q < kAdv; ++q) a += v.T(hi, q) < hk;
+            hi = v.move(hi, a);
+            if (a < kAdv) break;
+        }
+        // (not a constant: two reads side by side become one instruction, with
+        // the bank conflicts of a record: regular cadence, lags 8 samples apart,
+        // 4.43 ms with it, 2.61 without)
+        int one = 1;
+        asm("" : "+v"(one));
+        for (int rem = v.dist(i, hi); rem > 0; rem -= 2 * V::kUnit) {
+            const double d0 = v.T(i) - c, d1 = v.T(i, one) - c;  // (one past the window)
+            weigh(d0, 0);
+            if (rem > V::kUnit) weigh(d1, 1);
+            i = v.move(i, 2);
+        }
+        i = hi;
+    } else {
         double t = v.T(i), a1 = NUMER ? v.A(i, 1) : 0.0, a2 = WTD ? v.A(i, QW) : 0.0;
         while (t < hk) {
             const double d = t - c;  // FP64 difference
@@ -273,13 +323,7 @@ __device__ __forceinline__ void gauss_step(AccG<typename V::N>& acc, const V& v,
             t = v.T(i);
             if (NUMER) a1 = v.A(i, 1);
             if (WTD) a2 = v.A(i, QW);
-            double e;
-            if (E64) {
-                const double z = d * inv_h;
-                e = exp(-0.5 * z * z);
-            } else {
-                e = gauss_w32(d, k2);
-            }
+            const double e = gauss_w32(d, k2);
             bj += e;  // FP64 sums: windows of bursty samples hold thousands of points
             if (NUMER) Cj += e * b1;
             if (WTD) Bj += e * b2;
@@ -303,7 +347,7 @@ __device__ __forceinline__ void scan_gauss_lane(AccG<typename V::N>& acc, const 
     constexpr bool WTD = (F & WIN_WEIGHTED) != 0;
     if (ja >= jb) return;
     double s = gs[ja], vo = NUMER ? gvo[ja] : 0.0, wo = WTD ? gwo[ja] : 0.0;
-    typename V::P lo = v.lower(len, (s + delta) - W);
+    typename V::P lo = v.lower(len, (s + delta) - W), hi = lo;
     for (int j = ja; j < jb; ++j) {
         double s_n = 0.0, vo_n = 0.0, wo_n = 0.0;
         if (j + 1 < jb) {
@@ -311,7 +355,7 @@ __device__ __forceinline__ void scan_gauss_lane(AccG<typename V::N>& acc, const 
             if (NUMER) vo_n = gvo[j + 1];
             if (WTD) wo_n = gwo[j + 1];
         }
-        gauss_step<F>(acc, v, lo, s, vo, wo, delta, W, inv_h, k2);
+        gauss_step<F>(acc, v, lo, hi, s, vo, wo, delta, W, inv_h, k2);
         s = s_n;
         vo = vo_n;
         wo = wo_n;
@@ -436,11 +480,11 @@ __device__ __forceinline__ void scan_gauss_wave(AccG<typename V::N>& acc, const 
     const cdp cvo = NUMER ? uniform_ptr(gvo) : cs;
     const cdp cwo = WTD ? uniform_ptr(gwo) : cs;
     double s = cs[ja], vo = NUMER ? cvo[ja] : 0.0, wo = WTD ? cwo[ja] : 0.0;
-    typename V::P lo = v.lower(len, (s + delta) - W);
+    typename V::P lo = v.lower(len, (s + delta) - W), hi = lo;
     for (int j = ja; j < jb; ++j) {
         const int jn = min(j + 1, jb - 1);
         const double s_n = cs[jn], vo_n = NUMER ? cvo[jn] : 0.0, wo_n = WTD ? cwo[jn] : 0.0;
-        gauss_step<F>(acc, v, lo, s, vo, wo, delta, W, inv_h, k2);
+        gauss_step<F>(acc, v, lo, hi, s, vo, wo, delta, W, inv_h, k2);
         s = s_n;
         vo = vo_n;
         wo = wo_n;
