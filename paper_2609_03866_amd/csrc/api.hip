@@ -1886,7 +1886,12 @@ void CallRun::plan_window(WinLaunch& W) {
     W.item0.assign(ntask + 1, 0);
     W.wk0.assign(ntask + 1, 0);
     W.r0.assign(ntask + 1, 0);
-    std::vector<std::array<double, 3>> dens(ntask);  // window / outer density, extent
+    // estimated window range of J outer samples: range[i][0] J + range[i][1]
+    std::vector<std::array<double, 2>> range(ntask);
+    int64_t total = 0;
+    auto tiles_of = [](int64_t n, int32_t j) {  // (32-bit division where it serves)
+        return n < INT32_MAX ? (int64_t)(((uint32_t)n + j - 1) / (uint32_t)j) : ceil_div(n, j);
+    };
     std::vector<int32_t> Jtight(ntask, 0);
     for (int i = 0; i < ntask; ++i) {
         const WinPlan& P = W.plans[i];
@@ -1935,11 +1940,13 @@ void CallRun::plan_window(WinLaunch& W) {
         const double dens_o = (double)(dO.n - 1) / span_o;
         const int n_kt = (int)ceil_div(T.K, 64);
         const double ext = lext + 2.0 * T.W;
-        auto est = [&](int64_t j) { return dens_w * ((double)j / dens_o + ext) + 2.0; };
+        const double rj = dens_w / dens_o, r0 = dens_w * ext + 2.0;
+        range[i] = {rj, r0};
+        auto est = [&](int64_t j) { return rj * (double)j + r0; };
         // outer samples per workgroup: as many as keep the window range in
-        // LDS (half the capacity, for clustering)
-        int64_t Jt = 64;
-        while (Jt + 16 <= jmax && est(Jt + 16) <= 0.5 * cap) Jt += 16;
+        // LDS (half the capacity, for clustering), in steps of 16 from 64
+        const double steps = ((0.5 * cap - r0) / rj - 64.0) / 16.0;
+        int64_t Jt = 64 + (steps > 0.0 ? 16 * (int64_t)std::min(steps, (jmax - 64) / 16.0) : 0);
         while (Jt > 16 && est(Jt) > 0.5 * cap) Jt /= 2;
         T.J = (int32_t)Jt;
         // short of workspace: no more than about 2048 items per series, and
@@ -1953,7 +1960,7 @@ void CallRun::plan_window(WinLaunch& W) {
             Jtight[i] = (int32_t)q;
         }
         T.n_kt = n_kt;
-        dens[i] = {dens_w, dens_o, ext};
+        total += tiles_of(T.n_out, T.J) * n_kt;
         // algorithmic work: per (j, k) window, searches + per-point weight ops
         const double pts = rect ? 0.0 : dens_w * 2.0 * T.W;
         W.work += (double)dO.n * T.K * (8.0 + (rect ? 4.0 : 8.0 * pts));
@@ -1972,32 +1979,27 @@ void CallRun::plan_window(WinLaunch& W) {
     auto at_shift = [&](int32_t j) { return std::max(j >> shift, std::min(j, minJ)); };
     auto items = [&] {
         int64_t q = 0;
-        for (const WinTask& T : W.wt) q += ceil_div(T.n_out, at_shift(T.J)) * T.n_kt;
+        for (const WinTask& T : W.wt) q += tiles_of(T.n_out, at_shift(T.J)) * T.n_kt;
         return q;
     };
-    while (shift < 6 && items() < (rect ? 1024 : 4096)) ++shift;
-    if (items() < kWinItemsFew) {
+    for (; shift < 6 && total < (rect ? 1024 : 4096); total = items()) ++shift;
+    if (total < kWinItemsFew) {
         minJ = 4;
-        while (shift < 8 && items() < kWinItemsFew) ++shift;
+        for (total = items(); shift < 8 && total < kWinItemsFew; total = items()) ++shift;
     }
-    int64_t total = items();
-    for (WinTask& T : W.wt) {
-        int64_t Jt = at_shift(T.J);
-        if (J.tune.jscale > 0) Jt = std::min<int64_t>(Jt << J.tune.jscale, jmax);
-        if (J.tune.jscale < 0)
-            Jt = std::max<int64_t>(Jt >> -J.tune.jscale, std::min<int64_t>(Jt, 16));
-        T.J = (int32_t)Jt;
-    }
-    for (int i = 0; tight && i < ntask; ++i) W.wt[i].J = std::max(W.wt[i].J, Jtight[i]);
-    // the launch has one LDS size, set by the largest footprint
+    // the launch has one LDS size, set by the largest range
     double need = 0.0;
     int jneed = 16;
-    auto est_of = [&](int i, int64_t j) {
-        return dens[i][0] * ((double)j / dens[i][1] + dens[i][2]) + 2.0;
-    };
+    auto est_of = [&](int i, int64_t j) { return range[i][0] * (double)j + range[i][1]; };
     for (int i = 0; i < ntask; ++i) {
-        need = std::max(need, est_of(i, W.wt[i].J));
-        jneed = std::max(jneed, (int)W.wt[i].J);
+        WinTask& T = W.wt[i];
+        int32_t Jt = at_shift(T.J);
+        if (J.tune.jscale > 0) Jt = std::min(Jt << J.tune.jscale, jmax);
+        if (J.tune.jscale < 0) Jt = std::max(Jt >> -J.tune.jscale, std::min(Jt, 16));
+        if (tight) Jt = std::max(Jt, Jtight[i]);
+        T.J = Jt;
+        need = std::max(need, est_of(i, Jt));
+        jneed = std::max(jneed, (int)Jt);
     }
     // LDS: twice the estimated window range (clustering margin), rounded up
     const int want = (int)std::min<double>(cap, round_up((int64_t)(2.0 * need) + 64, 64));
@@ -2006,6 +2008,7 @@ void CallRun::plan_window(WinLaunch& W) {
     // items of few lags (e.g. the lag-0 scale tasks) grow within that
     // footprint until they hold ~8192 windows: a workgroup's searches and
     // staging cost the same for any size (while the launch keeps enough)
+    int64_t tiles = 0;
     for (int i = 0; i < ntask; ++i) {
         WinTask& T = W.wt[i];
         const int64_t kin = std::min<int64_t>(T.K, 64);
@@ -2017,22 +2020,18 @@ void CallRun::plan_window(WinLaunch& W) {
             Jt *= 2;
         }
         T.J = (int32_t)Jt;
+        T.n_jt = (int32_t)tiles_of(T.n_out, T.J);
+        tiles += (int64_t)T.n_jt * T.n_kt;
     }
     // j-tiles per work item: one item per tile while that leaves the
     // launch few items; more tiles per item (one partial per group of
     // tiles) when the launch has many
-    int64_t tiles = 0;
-    for (int i = 0; i < ntask; ++i) {
-        WinTask& T = W.wt[i];
-        T.n_jt = (int32_t)ceil_div(T.n_out, T.J);
-        tiles += (int64_t)T.n_jt * T.n_kt;
-    }
     const int G = (int)std::max<int64_t>(1, std::min<int64_t>(kWinGroupMax,
                                                               tiles / kWinItemsMin));
     for (int i = 0; i < ntask; ++i) {
         WinTask& T = W.wt[i];
         T.G = G;
-        T.n_jg = (int32_t)ceil_div(T.n_jt, G);
+        T.n_jg = (T.n_jt + G - 1) / G;
         T.item0 = W.nitems;
         W.item0[i] = W.nitems;
         W.wk0[i] = W.total_rows;
@@ -2044,11 +2043,15 @@ void CallRun::plan_window(WinLaunch& W) {
     W.item0[ntask] = W.nitems;
     W.wk0[ntask] = W.total_rows;
     W.r0[ntask] = W.nred1;
-    bool few = ntask <= kWinFewTasks;
-    for (const WinTask& T : W.wt) few = few && T.n_jg <= kWinFewGroups && T.K > 0;
     W.few = 0;
-    if (few)
-        for (const WinTask& T : W.wt) W.few += T.n_kt;
+    if (ntask <= kWinFewTasks) {
+        bool few = true;
+        for (const WinTask& T : W.wt) {
+            few = few && T.n_jg <= kWinFewGroups && T.K > 0;
+            W.few += T.n_kt;
+        }
+        if (!few) W.few = 0;
+    }
 }
 
 // every array that a window pass reads must exist: checked on the host
