@@ -1987,7 +1987,14 @@ void CallRun::plan_window(WinLaunch& W) {
         minJ = 4;
         for (total = items(); shift < 8 && total < kWinItemsFew; total = items()) ++shift;
     }
-    // the launch has one LDS size, set by the largest range
+    // Tiles of one length where the last would be nearly empty, or where the tiles
+    // of a series come to every CU in the same place (their number times the lag
+    // tiles divides an XCD's 32 CUs), so that some CUs would scan only long tiles
+    // and others only short ones (4000 weighted series of 448 samples, tiles of
+    // 432 and 16: 3.07 ms the call, of 224: 1.92; of 560, 432 and 128: 3.09, of
+    // 288: 2.33). Else the longer ones are kept (10,000 rectangle series, 208, 208
+    // and 84: 1.89 ms, even ones 1.96).
+    // The launch has one LDS size, set by the largest range.
     double need = 0.0;
     int jneed = 16;
     auto est_of = [&](int i, int64_t j) { return range[i][0] * (double)j + range[i][1]; };
@@ -1996,6 +2003,12 @@ void CallRun::plan_window(WinLaunch& W) {
         int32_t Jt = at_shift(T.J);
         if (J.tune.jscale > 0) Jt = std::min(Jt << J.tune.jscale, jmax);
         if (J.tune.jscale < 0) Jt = std::max(Jt >> -J.tune.jscale, std::min(Jt, 16));
+        if (Jt >= 16 && T.n_out > Jt) {
+            const int64_t n = tiles_of(T.n_out, Jt), per = n * T.n_kt;
+            const int64_t rem = T.n_out - (n - 1) * Jt;
+            if (rem < Jt / 4 || (per <= 32 && 32 % per == 0))
+                Jt = std::min(Jt, (int32_t)round_up(ceil_div(T.n_out, n), 16));
+        }
         if (tight) Jt = std::max(Jt, Jtight[i]);
         T.J = Jt;
         need = std::max(need, est_of(i, Jt));
