@@ -1874,13 +1874,18 @@ void CallRun::plan_window(WinLaunch& W) {
     const int arrays = 1 + ((W.plans.empty() ? false : ((wflags & WIN_NUMER) != 0)) ? 1 : 0) +
                        (weighted ? (rect ? 2 : 1) : 0);
     const int jmax = 1024;
-    // LDS per workgroup (doubles): the staged window arrays (the outer
-    // samples stay in global memory). 18 KB leave the rectangle scan its eight
-    // waves per SIMD; the Gaussian scan has registers for six, 24 KB (2048
-    // rectangle pairs: 24 KB 21.4 ms, 18 KB 19.4; 10,000 weighted series: 64.0,
-    // 65.9 ms)
-    int cap = (rect ? 18 * 1024 / 8 / arrays : gauss_entry(arrays)) - 8;
-    cap = std::max(256, std::min(4096, cap));
+    // LDS per workgroup (doubles): the staged window arrays (the outer samples
+    // stay in global memory), 24 KB: the Gaussian scan has registers for six
+    // waves per SIMD. The unweighted rectangle scan has them for eight, which 18
+    // KB leave it (2048 pairs: 24 KB 21.4 ms, 18 KB 19.4), and the weighted one is
+    // no slower with tiles for 18 KB, staged in up to 24. But launches of wide
+    // windows are planned for 24 KB: those whose tile would be short in 18, or
+    // would not fit at all (200 series of 20,000 samples, 18 and 24 KB: 64 lags
+    // over 500 samples 1.03, 0.92 ms, 650 1.88, 1.01, 1000 2.03, 2.40, 1400 9.39,
+    // 2.56; with weights 250 1.85, 1.28, 350 2.79, 1.91, 650 7.67, 3.12).
+    const int room = rect ? 24 * 1024 / 8 / arrays : gauss_entry(arrays);
+    int cap = std::max(256, std::min(4096, room - 8));
+    const int cap18 = std::max(256, 18 * 1024 / 8 / arrays - 8);
     const int ntask = (int)W.plans.size();
     W.wt.assign(ntask, WinTask{});
     W.item0.assign(ntask + 1, 0);
@@ -1892,7 +1897,8 @@ void CallRun::plan_window(WinLaunch& W) {
     auto tiles_of = [](int64_t n, int32_t j) {  // (32-bit division where it serves)
         return n < INT32_MAX ? (int64_t)(((uint32_t)n + j - 1) / (uint32_t)j) : ceil_div(n, j);
     };
-    std::vector<int32_t> Jtight(ntask, 0);
+    std::vector<int32_t> Jtight(ntask, 0), Jwide(rect ? ntask : 0);
+    double windows = 0.0, wide = 0.0;  // outer samples x lags; those of wide windows
     for (int i = 0; i < ntask; ++i) {
         const WinPlan& P = W.plans[i];
         const SeriesSet& SW = J.set[P.wi_set];
@@ -1945,10 +1951,20 @@ void CallRun::plan_window(WinLaunch& W) {
         auto est = [&](int64_t j) { return rj * (double)j + r0; };
         // outer samples per workgroup: as many as keep the window range in
         // LDS (half the capacity, for clustering), in steps of 16 from 64
-        const double steps = ((0.5 * cap - r0) / rj - 64.0) / 16.0;
-        int64_t Jt = 64 + (steps > 0.0 ? 16 * (int64_t)std::min(steps, (jmax - 64) / 16.0) : 0);
-        while (Jt > 16 && est(Jt) > 0.5 * cap) Jt /= 2;
-        T.J = (int32_t)Jt;
+        auto fit = [&](int c) {
+            const double steps = ((0.5 * c - r0) / rj - 64.0) / 16.0;
+            int64_t Jt =
+                64 + (steps > 0.0 ? 16 * (int64_t)std::min(steps, (jmax - 64) / 16.0) : 0);
+            while (Jt > 16 && est(Jt) > 0.5 * c) Jt /= 2;
+            return (int32_t)Jt;
+        };
+        T.J = fit(rect ? cap18 : cap);
+        if (rect) {
+            Jwide[i] = fit(cap);
+            windows += (double)dO.n * T.K;
+            if ((T.J < 128 && Jwide[i] > T.J) || est(16) > 0.9 * cap18)
+                wide += (double)dO.n * T.K;
+        }
         // short of workspace: no more than about 2048 items per series, and
         // ranges past the stage scanned from memory
         if (tight) {
@@ -1960,11 +1976,20 @@ void CallRun::plan_window(WinLaunch& W) {
             Jtight[i] = (int32_t)q;
         }
         T.n_kt = n_kt;
-        total += tiles_of(T.n_out, T.J) * n_kt;
+        total += tiles_of(T.n_out, T.J) * n_kt;  // (planned again below for wide windows)
         // algorithmic work: per (j, k) window, searches + per-point weight ops
         const double pts = rect ? 0.0 : dens_w * 2.0 * T.W;
         W.work += (double)dO.n * T.K * (8.0 + (rect ? 4.0 : 8.0 * pts));
         W.wt[i] = T;
+    }
+    if (wide > windows / 16.0) {  // a few wide ones: 18 KB, and their ranges from memory
+        total = 0;
+        for (int i = 0; i < ntask; ++i) {
+            W.wt[i].J = Jwide[i];
+            total += tiles_of(W.wt[i].n_out, Jwide[i]) * W.wt[i].n_kt;
+        }
+    } else if (rect && !weighted) {
+        cap = cap18;
     }
     // ... and fewer, down to 16, while the launch has less than 1024 (rectangle)
     // or 4096 items, then down to one per wave while it has less than
