@@ -1434,7 +1434,11 @@ class CallRun {
     std::vector<double*> fparts, numer, bspec, spart, bunw;
     int64_t ntiles_all = 0;
     bool bounds_pass = false;
-    bool tight = false;  // the workspace did not fit: window items as long as they may be
+    // the workspace did not fit: 1, window items at least as long as 2048 per
+    // series make them, and no more than kWinItemsMin by grouping tiles; 2, tiles
+    // grouped as far as they may be, so that no call needs more than with items
+    // sized series by series (powers of two, tiles / kWinItemsMin in a group)
+    int tight = 0;
     bool short_of_ws(int rc) const {
         return rc == NCF_E_NOMEM || (R.fixed_dev && rc == NCF_E_UNSUPPORTED);
     }
@@ -1886,6 +1890,7 @@ void CallRun::plan_window(WinLaunch& W) {
     const int room = rect ? 24 * 1024 / 8 / arrays : gauss_entry(arrays);
     int cap = std::max(256, std::min(4096, room - 8));
     const int cap18 = std::max(256, 18 * 1024 / 8 / arrays - 8);
+    const int cap_t = std::max(256, 24 * 1024 / 8 / arrays - 8);  // (see Jtight)
     const int ntask = (int)W.plans.size();
     W.wt.assign(ntask, WinTask{});
     W.item0.assign(ntask + 1, 0);
@@ -1965,15 +1970,13 @@ void CallRun::plan_window(WinLaunch& W) {
             if ((T.J < 128 && Jwide[i] > T.J) || est(16) > 0.9 * cap18)
                 wide += (double)dO.n * T.K;
         }
-        // short of workspace: no more than about 2048 items per series, and
-        // ranges past the stage scanned from memory
+        // short of workspace: no more than about 2048 items per series
         if (tight) {
-            const int cap_t = std::max(256, 24 * 1024 / 8 / arrays - 8);
-            int64_t q = 64;
+            int32_t q = 64;
             while (q * 2 <= jmax && est(q * 2) <= 0.5 * cap_t &&
                    (double)dO.n * n_kt / (double)(q * 2) >= 2048.0)
                 q *= 2;
-            Jtight[i] = (int32_t)q;
+            Jtight[i] = J.tune.jscale > 0 ? std::min(q << J.tune.jscale, jmax) : q;
         }
         T.n_kt = n_kt;
         total += tiles_of(T.n_out, T.J) * n_kt;  // (planned again below for wide windows)
@@ -1988,7 +1991,7 @@ void CallRun::plan_window(WinLaunch& W) {
             W.wt[i].J = Jwide[i];
             total += tiles_of(W.wt[i].n_out, Jwide[i]) * W.wt[i].n_kt;
         }
-    } else if (rect && !weighted) {
+    } else if (rect && !weighted && !tight) {
         cap = cap18;
     }
     // ... and fewer, down to 16, while the launch has less than 1024 (rectangle)
@@ -2034,14 +2037,15 @@ void CallRun::plan_window(WinLaunch& W) {
             if (rem < Jt / 4 || (per <= 32 && 32 % per == 0))
                 Jt = std::min(Jt, (int32_t)round_up(ceil_div(T.n_out, n), 16));
         }
-        if (tight) Jt = std::max(Jt, Jtight[i]);
         T.J = Jt;
+        if (tight) Jt = std::max(Jt, Jtight[i]);
         need = std::max(need, est_of(i, Jt));
         jneed = std::max(jneed, (int)Jt);
     }
     // LDS: twice the estimated window range (clustering margin), rounded up
-    const int want = (int)std::min<double>(cap, round_up((int64_t)(2.0 * need) + 64, 64));
-    W.cap = std::max(256, want);
+    const int64_t want = round_up((int64_t)(2.0 * need) + 64, 64);
+    W.cap = std::max(256, (int)std::min<double>(cap, want));
+    const int grow_t = std::max(256, (int)std::min<double>(cap_t, want));
     const int64_t jtop = round_up(jneed, 64);
     // items of few lags (e.g. the lag-0 scale tasks) grow within that
     // footprint until they hold ~8192 windows: a workgroup's searches and
@@ -2057,6 +2061,12 @@ void CallRun::plan_window(WinLaunch& W) {
             total -= own(Jt) - own(Jt * 2);
             Jt *= 2;
         }
+        if (tight) {
+            int64_t q = Jtight[i];
+            while (q * 2 <= jtop && est_of(i, q * 2) <= 0.5 * grow_t && q * 2 * kin <= 8192)
+                q *= 2;
+            Jt = std::max(Jt, q);
+        }
         T.J = (int32_t)Jt;
         T.n_jt = (int32_t)tiles_of(T.n_out, T.J);
         tiles += (int64_t)T.n_jt * T.n_kt;
@@ -2064,8 +2074,12 @@ void CallRun::plan_window(WinLaunch& W) {
     // j-tiles per work item: one item per tile while that leaves the
     // launch few items; more tiles per item (one partial per group of
     // tiles) when the launch has many
-    const int G = (int)std::max<int64_t>(1, std::min<int64_t>(kWinGroupMax,
-                                                              tiles / kWinItemsMin));
+    // (short of workspace: no more items than that, then the fewest there are)
+    const int G = tight == 2 ? kWinGroupMax
+                             : (int)std::max<int64_t>(
+                                   1, std::min<int64_t>(kWinGroupMax,
+                                                        tight ? ceil_div(tiles, kWinItemsMin)
+                                                              : tiles / kWinItemsMin));
     for (int i = 0; i < ntask; ++i) {
         WinTask& T = W.wt[i];
         T.G = G;
@@ -2310,9 +2324,9 @@ int CallRun::alloc_phase2() {
         bounds_pass = ntiles_all > 4096;
         rc = ensure2();
     }
-    if (short_of_ws(rc) && ntw > 0) {  // with fewer, longer window items
+    while (short_of_ws(rc) && ntw > 0 && tight < 2) {  // with fewer, longer window items
         clear_error();
-        tight = true;
+        ++tight;
         replan_window(W1);
         J.info_window_items = W1.nitems;
         rc = ensure2();
@@ -2906,9 +2920,9 @@ int CallRun::separate3() {
     if (ntw2 > 0) {
         void* ws3 = nullptr;
         int rc = ensure_ws(R, 2, a3.off + 256, &ws3);
-        if (short_of_ws(rc) && !tight) {  // with fewer, longer window items
+        while (short_of_ws(rc) && tight < 2) {  // with fewer, longer window items
             clear_error();
-            tight = true;
+            ++tight;
             replan_window(W2);
             a3 = Arena{};
             layout3(a3);
