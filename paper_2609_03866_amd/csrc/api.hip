@@ -519,6 +519,7 @@ struct Job {
     // filled by run_job: what the call planned
     int64_t info_grid_cells = 0, info_window_items = 0;
     int info_grids = 0, info_window_launches = 0;
+    int info_fft_grids = 0;   // grids whose transforms take Tune::fft
     int info_fold_grids = 0;  // grids read off a lag lattice
 };
 
@@ -800,8 +801,8 @@ int run_regular(Job& J, const std::vector<SeriesDesc>& sdesc,
             continue;
         }
         // the fused route serves one real pair of channels (values and
-        // counts); plans take it as well, the autotuner's transform variants
-        // apply to the general one
+        // counts); plans take it as well (the autotuner's transform variants
+        // apply to the general one only, and are not timed where it is unused)
         rp.fused = mode == 0 && reg_fused(J.set[0].offs[p + 1] - J.set[0].offs[p], rp.G, rp.Q,
                                           rp.N);
         rps.push_back(rp);
@@ -816,6 +817,7 @@ int run_regular(Job& J, const std::vector<SeriesDesc>& sdesc,
     const int nfus = nreg - ngen;
     if (mode == 0 && ngen > 0) NCF_TRY(emit(J, standardize));
     J.info_grids = nreg;
+    J.info_fft_grids = ngen;  // (the fused passes have their own radices)
     J.info_grid_cells = 0;
     for (auto& rp : rps) J.info_grid_cells += rp.N;
     J.info_window_items = 0;
@@ -2197,7 +2199,7 @@ int CallRun::plan_spectral() {
     }
     nts = (int)splans.size();
     Keval = (int)(J.ccf ? K : K + 1);
-    J.info_grids = nts;
+    J.info_grids = J.info_fft_grids = nts;
     J.info_grid_cells = 0;
     J.info_fold_grids = 0;
     for (auto& sp : splans) {
@@ -3647,7 +3649,7 @@ struct ncf_plan_s {
     std::vector<int32_t> hstatus;          // host statuses (host-pointer plans)
     // what was planned, and how (ncf_plan_info)
     ncf::Tune tune;
-    int grids = 0, window_launches = 0, fold_grids = 0;
+    int grids = 0, fft_grids = 0, window_launches = 0, fold_grids = 0;
     int64_t grid_cells = 0, window_items = 0;
     int autotuned = 0, candidates = 0;
     int tune_cached = 0;  // autotuned settings read from the autotune cache
@@ -3746,6 +3748,7 @@ int plan_build(ncf_plan_s* P, Job& J, const double* const* tin, const double* co
     NCF_TRY(run_job(B, tdev, xdev, edev));
     P->tune = tune;
     P->grids = B.info_grids;
+    P->fft_grids = B.info_fft_grids;
     P->fold_grids = B.info_fold_grids;
     P->grid_cells = B.info_grid_cells;
     P->window_items = B.info_window_items;
@@ -4015,7 +4018,7 @@ int plan_create(Job& J, const double* const* tin, const double* const* ein, ncf_
         }
         if (best->grids > 0) {
             for (int sp : {1, 2}) {
-                if (rc != NCF_OK) break;
+                if (rc != NCF_OK || best->fft_grids == 0) break;
                 Tune t = best->tune;
                 t.fft.split = sp;
                 rc = attempt(t);
