@@ -153,10 +153,10 @@ __device__ __forceinline__ void dft4(C2& a0, C2& a1, C2& a2, C2& a3, int sign) {
 }
 
 // multiply by w_16^m (m in 0..15) for the given sign; constants fold.
-// YF: the imaginary part of m <= 4 as fma(y, wr, x wi). The compiler chooses
-// which product of cmul's x wi + y wr it contracts by the code around it, and
-// takes this form in the first stage of the plain pass: the pass that is
-// fused with the spread states it, so that both round alike.
+// YF: the imaginary part of m <= 4 as fma(y, wr, x wi). Which product of
+// cmul's x wi + y wr the compiler contracts depends on the code around it, so
+// the first stages of the plain FP32 pass and of the pass that is fused with the
+// spread, which are to round alike, both state it.
 template <bool YF = false, typename C2>
 __device__ __forceinline__ C2 mul_w16(C2 a, int m, int sign) {
     typedef decltype(a.x) R;
@@ -354,8 +354,8 @@ __device__ __forceinline__ void run_stages(const PassArgs& a, C2* lds, C2* gbase
     constexpr int nst = n16 + (rem ? 1 : 0);
     if constexpr (ST < nst) {
         constexpr int RX = ST < n16 ? 16 : (1 << rem);
-        stockham_stage<RX, ST == 0, ST == nst - 1, LGR, NS, LGT>(a, lds, gbase, s0,
-                                                                  (int)threadIdx.x);
+        stockham_stage<RX, ST == 0, ST == nst - 1, LGR, NS, LGT, 16, (sizeof(C2) == 8)>(
+            a, lds, gbase, s0, (int)threadIdx.x);
         run_stages<LGR, ST + 1, NS * RX, LGT>(a, lds, gbase, s0);
     }
 }
