@@ -214,8 +214,9 @@ struct PtsLds {
 // for the sample at offset x from the first cell, by e[q + 1] = e[q] r[q],
 // r[q + 1] = r[q] exp(2 k2) from two exponentials instead of kRun (40 FP64
 // instructions each): 1000 series, spread and first pass 1.75 -> 1.28 ms.
-// The recurrence adds at most (q + q^2 / 2) 2^-53 to a weight, 3e-15 over a run
-// of 8, beside the kernel's truncation at 1e-13. Weights past the support
+// Relative error of a weight, mostly that of its exponents k2 x^2 and k2 (1 - 2 x):
+// 5e-15 near the peak, up to 2e-14 at the edge of the support (an exponential
+// per weight: 1.1e-14 there), beside the kernel's truncation at 1e-13. Weights past the support
 // |d| <= W, all below that truncation, are left in; with them the type-1 sums are
 // nearer to the exact ones (worst mode, oversampling 1.25: 2.8e-4 -> 3.8e-6 of
 // sum |v|; 1.5: 2.7e-10 -> 3.0e-12; 2: 3.2e-13 -> 1.3e-13; 3.9: 1.2e-13, 1.3e-13).
@@ -454,8 +455,10 @@ __device__ __forceinline__ void gather_run(R (&acc)[CPT], R (&accu)[CPT],
     const gptr<const double> t = gbl(t_);
     const R c2 = sizeof(R) == 8 ? exp(2.0 * k2) : (R)0;
     const int reach = (int)W + 2;
-    const int64_t blo = (cell0 - reach) >> 4;  // floor
-    const int64_t bhi = ((cell0 + CPT - 1 + reach) >> 4) + 1;
+    constexpr int lgIdx = __builtin_ctz(kCellIdx);
+    static_assert(kCellIdx == 1 << lgIdx, "table entries by shifts (floor)");
+    const int64_t blo = (cell0 - reach) >> lgIdx;
+    const int64_t bhi = ((cell0 + CPT - 1 + reach) >> lgIdx) + 1;
     const int i0 = tab[blo > 0 ? blo : 0], i1 = tab[bhi < nb ? bhi : nb];
     const R W2 = W * W;
     for (int ib = i0; ib < i1; ib += 4) {

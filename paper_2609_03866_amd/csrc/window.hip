@@ -47,7 +47,6 @@ extern __shared__ double g_win_lds[];
 typedef __attribute__((address_space(1))) const double* gdp;
 
 constexpr double kInf = __builtin_huge_val();
-constexpr double kNan = __builtin_nan("");
 
 // Fallback when the window range does not fit in LDS: global memory with
 // explicit bounds.
@@ -369,7 +368,7 @@ __device__ __forceinline__ void scan_gauss_lane(AccG<typename V::N>& acc, const 
 // after it moves; an outer sample whose window does not move costs two
 // compares. Counts accumulate as address differences and a prefix value is
 // read at a fixed distance from its bound. Same predicates and the same
-// order of the numerator sums as scan_lane. The outer samples (s_j, vo_j,
+// order of the numerator sums as scan_rect_glb. The outer samples (s_j, vo_j,
 // wo_j) are not staged: they come from global memory.
 struct AccR {
     double C, B;
