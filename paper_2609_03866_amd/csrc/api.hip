@@ -1900,6 +1900,7 @@ void CallRun::plan_window(WinLaunch& W) {
     W.r0.assign(ntask + 1, 0);
     // estimated window range of J outer samples: range[i][0] J + range[i][1]
     std::vector<std::array<double, 2>> range(ntask);
+    double out_lags = 0.0, lags_tile = 1.0;  // outer samples x lags; the fullest lag tile
     int64_t total = 0;
     auto tiles_of = [](int64_t n, int32_t j) {  // (32-bit division where it serves)
         return n < INT32_MAX ? (int64_t)(((uint32_t)n + j - 1) / (uint32_t)j) : ceil_div(n, j);
@@ -1981,41 +1982,68 @@ void CallRun::plan_window(WinLaunch& W) {
             Jtight[i] = J.tune.jscale > 0 ? std::min(q << J.tune.jscale, jmax) : q;
         }
         T.n_kt = n_kt;
-        total += tiles_of(T.n_out, T.J) * n_kt;  // (planned again below for wide windows)
+        out_lags += (double)T.n_out * T.K;
+        lags_tile = std::max(lags_tile, (double)T.K / n_kt);
         // algorithmic work: per (j, k) window, searches + per-point weight ops
         const double pts = rect ? 0.0 : dens_w * 2.0 * T.W;
         W.work += (double)dO.n * T.K * (8.0 + (rect ? 4.0 : 8.0 * pts));
         W.wt[i] = T;
     }
     if (wide > windows / 16.0) {  // a few wide ones: 18 KB, and their ranges from memory
-        total = 0;
-        for (int i = 0; i < ntask; ++i) {
-            W.wt[i].J = Jwide[i];
-            total += tiles_of(W.wt[i].n_out, Jwide[i]) * W.wt[i].n_kt;
-        }
+        for (int i = 0; i < ntask; ++i) W.wt[i].J = Jwide[i];
     } else if (rect && !weighted && !tight) {
         cap = cap18;
     }
-    // ... and fewer, down to 16, while the launch has less than 1024 (rectangle)
-    // or 4096 items, then down to one per wave while it has less than
-    // kWinItemsFew (four per CU). An item's staging and searches cost as much as a
-    // few dozen of its outer samples, so a launch that fills the chip wants the
-    // fewest items (2048 or more per series: 10,000 weighted series 70.8 ms, 2048
-    // rectangle pairs 24.5 ms; by this rule 64.0, 19.4), one that does not the
-    // shortest (2000 samples, 101 lags: 64 per item 86 us, 16 75, 4 73). In
-    // between (100,000 samples, 401 lags, 1024 and 4096 items): Gaussian 262, 241
-    // us, rectangle 122, 134.
-    int minJ = 16, shift = 0;
-    auto at_shift = [&](int32_t j) { return std::max(j >> shift, std::min(j, minJ)); };
-    auto items = [&] {
-        int64_t q = 0;
-        for (const WinTask& T : W.wt) q += tiles_of(T.n_out, at_shift(T.J)) * T.n_kt;
-        return q;
+    // ... and fewer. An item's staging and searches cost as much as a few dozen
+    // of its outer samples, so a launch that fills the chip many times over wants
+    // few items (2048 or more per series: 10,000 weighted series 70.8 ms, 2048
+    // rectangle pairs 24.5 ms; by this rule 63.7, 19.5), one that does not the
+    // shortest (2000 samples, 101 lags: 64 per item 86 us, 16 75, 4 73) that one
+    // round of the chip holds. In between, items are 64 samples long while that
+    // leaves the launch, or the series alone, more than a few thousand: by the
+    // range alone, uniform batches are no faster (100 series of 2000 samples, 128
+    // lags: 67 us of scan at 64 and at 352) and series in bursts slower (24 FP64
+    // pairs of 16,000 samples in bursts, 57 lags: 12.0 ms at 64, 17.3 at 128).
+    // Tasks of an eighth of the launch's lags (the lag-0 scales) stay longer.
+    //   up to: 64, or as many as leave 16,384 (rectangle 4096) items in the launch,
+    //   or 1024 to 8192 (512 to 1024) in the series, by its lags;
+    //   down to: 2048 (1024) items in the launch, but 16 samples, and one per run;
+    //   where that leaves less than kWinItemsFew: one per wave.
+    // An item of less than 33 lags has as many runs of outer samples as they leave
+    // lanes for: a length below their number leaves lanes idle (2338 samples in
+    // bursts, one lag: 64 per item 653 us, 4 1492, 256 480), and one that is no
+    // multiple of it a part-filled round.
+    auto runs_of = [](const WinTask& T) {  // (see window_item)
+        int lanes = 1;
+        while (lanes < std::min(T.K, 64)) lanes *= 2;
+        return 256 / lanes;
     };
-    for (; shift < 6 && total < (rect ? 1024 : 4096); total = items()) ++shift;
-    if (total < kWinItemsFew) {
-        minJ = 4;
-        for (total = items(); shift < 8 && total < kWinItemsFew; total = items()) ++shift;
+    int shortest = 16;
+    const double tiles_all = out_lags / lags_tile;
+    auto longest = [&](const WinTask& T) {
+        const double lags = (double)T.K / T.n_kt;
+        if (lags < lags_tile / 8.0) return rect ? 512 : 256;
+        const double own = (double)T.n_out * T.n_kt /
+                           (rect ? std::max(512.0, 16.0 * lags) : std::max(1024.0, 128.0 * lags));
+        return (int32_t)std::min((double)jmax,
+                                 std::max({64.0, tiles_all / (rect ? 4096.0 : 16384.0), own}));
+    };
+    int32_t top = (int32_t)std::min((double)jmax, std::ceil(tiles_all / (rect ? 1024.0 : 2048.0)));
+    auto length = [&](const WinTask& T) {
+        const int runs = runs_of(T);
+        int32_t j = std::min(std::min(T.J, longest(T)), std::max({top, runs, shortest}));
+        j = (j + 3) & ~3;
+        const int m = (j + runs - 1) / runs;
+        return m > 1 && j < 0.85 * m * runs ? (m - 1) * runs : j;
+    };
+    auto items = [&] {  // as many of the fullest lag tiles
+        double q = 0.0;
+        for (const WinTask& T : W.wt) q += (double)tiles_of(T.n_out, length(T)) * T.K;
+        return q / lags_tile;
+    };
+    if (tiles_all < (double)jmax * kWinItemsFew && items() < kWinItemsFew) {
+        shortest = 4;
+        top = (int32_t)std::min((double)jmax, std::ceil(tiles_all / kWinItemsFew));
     }
     // Tiles of one length where the last would be nearly empty, or where the tiles
     // of a series come to every CU in the same place (their number times the lag
@@ -2024,29 +2052,32 @@ void CallRun::plan_window(WinLaunch& W) {
     // 432 and 16: 3.07 ms the call, of 224: 1.92; of 560, 432 and 128: 3.09, of
     // 288: 2.33). Else the longer ones are kept (10,000 rectangle series, 208, 208
     // and 84: 1.89 ms, even ones 1.96).
-    // The launch has one LDS size, set by the largest range.
     double need = 0.0;
     int jneed = 16;
     auto est_of = [&](int i, int64_t j) { return range[i][0] * (double)j + range[i][1]; };
     for (int i = 0; i < ntask; ++i) {
         WinTask& T = W.wt[i];
-        int32_t Jt = at_shift(T.J);
+        int32_t Jt = length(T);
         if (J.tune.jscale > 0) Jt = std::min(Jt << J.tune.jscale, jmax);
         if (J.tune.jscale < 0) Jt = std::max(Jt >> -J.tune.jscale, std::min(Jt, 16));
         if (Jt >= 16 && T.n_out > Jt) {
             const int64_t n = tiles_of(T.n_out, Jt), per = n * T.n_kt;
             const int64_t rem = T.n_out - (n - 1) * Jt;
             if (rem < Jt / 4 || (per <= 32 && 32 % per == 0))
-                Jt = std::min(Jt, (int32_t)round_up(ceil_div(T.n_out, n), 16));
+                Jt = std::min(Jt, (int32_t)round_up(ceil_div(T.n_out, n), runs_of(T)));
         }
         T.J = Jt;
+        total += tiles_of(T.n_out, Jt) * T.n_kt;
         if (tight) Jt = std::max(Jt, Jtight[i]);
         need = std::max(need, est_of(i, Jt));
         jneed = std::max(jneed, (int)Jt);
     }
-    // LDS: twice the estimated window range (clustering margin), rounded up
+    // The launch stages as much as its slots leave room for, also where the
+    // estimate is smaller: series in bursts hold more, and their ranges that do not
+    // fit are read from memory. Short of workspace items grow within twice the
+    // estimate.
+    W.cap = cap;
     const int64_t want = round_up((int64_t)(2.0 * need) + 64, 64);
-    W.cap = std::max(256, (int)std::min<double>(cap, want));
     const int grow_t = std::max(256, (int)std::min<double>(cap_t, want));
     const int64_t jtop = round_up(jneed, 64);
     // items of few lags (e.g. the lag-0 scale tasks) grow within that

@@ -324,9 +324,9 @@ constexpr int kWinJc = 64;          // j-groups per first-level reduction block
 constexpr int kWinGroupMax = 16;    // most j-tiles per window work item
 constexpr int kWinItemsFew = 1024;   // items that a launch should have (see plan_window)
 // Launches of at most kWinFewTasks tasks of at most kWinFewGroups j-groups each are
-// reduced by one kernel: 10 partials per wave take 6 us, 32 take 13, the two
-// launches 8 to 9.
-constexpr int kWinFewTasks = 16, kWinFewGroups = 192;
+// reduced by one kernel: 10 partials per wave take 6 us, 16 take 7, 32 take 13, the
+// two launches 8 to 9.
+constexpr int kWinFewTasks = 16, kWinFewGroups = 256;
 constexpr int kWinItemsMin = 16384; // items a launch keeps before grouping j-tiles
 
 // --------------------------------------------------- A2-A6 spectral route
