@@ -49,9 +49,11 @@ __global__ void k_reg_clear(const RegTask* __restrict__ tasks, int ntasks) {
     if (i < ntasks) *gbl(tasks[i].bad) = 0;
 }
 
-// Samples of one cell that the lane that sums them reads at once (general fill,
-// 60,000 cells of 16 samples, the call: 482 us one at a time, 376 so; fused, 500
-// cells of 64: 1543, 1251).
+// Samples of one cell that the lane that sums them reads at once, past the second
+// (general fill, 60,000 cells of 16 samples, the call: 482 us one at a time, 376 so;
+// fused, 500 cells of 64: 1543, 1251; the second by itself: most cells have one, and
+// a lattice batch of 143 M cells takes 1.46 ms in the first passes instead of 1.27
+// where each reads four).
 constexpr int kRunLoads = 4;
 
 // One workgroup fills kRegCells lattice cells of every input grid of one
@@ -117,8 +119,9 @@ k_reg_fill(const RegTask* __restrict__ tasks, const int64_t* __restrict__ blk0, 
                 continue;
             }
             if (i > i0 && lat(t[i - 1]) == mr) continue;  // not first
-            double sv = 0.0, sw = 0.0, sn = 0.0;
-            for (int64_t j = i; j < i1;) {
+            double sv = 0.0 + v[i], sw = WT && wp ? w[i] : 1.0, sn = 1.0;
+            // the other samples of the cell, in order
+            for (int64_t j = i + 1 < i1 && lat(t[i + 1]) == mr ? i + 1 : i1; j < i1;) {
                 double tj[kRunLoads], vj[kRunLoads], wj[kRunLoads];
 #pragma unroll
                 for (int q = 0; q < kRunLoads; ++q) {
@@ -199,20 +202,31 @@ k_reg_seg(const RegTask* __restrict__ tasks, const int64_t* __restrict__ blk0, i
     };
     const int32_t nseg = (int32_t)((T.G + kRegSegCells - 1) / kRegSegCells);
     const int tid = threadIdx.x, lane = tid & 63;
+    // a wave's samples in a row, all of its loads at once
+    constexpr int kRounds = kMomentChunk / kThreads;
+    const int64_t w0 = i0 + (tid >> 6) * (64 * kRounds);
+    double tv[kRounds];
+#pragma unroll
+    for (int u = 0; u < kRounds; ++u) tv[u] = t[min(w0 + 64 * u + lane, i1 - 1)];
+    const double tb = t[max(min(w0, i1) - 1, (int64_t)0)];
     if (tid == 0) ngap = 0;
     __syncthreads();
-    for (int64_t r = i0; r < i1; r += kThreads) {
-        const int64_t i = r + tid;
+    int32_t before = w0 > 0 ? block_of(tb) : -1;  // of the sample before the round
+#pragma unroll
+    for (int u = 0; u < kRounds; ++u) {
+        const int64_t r = w0 + 64 * u, i = r + lane;
         const bool live = i < i1;
-        const int32_t e = live ? block_of(t[i]) : -1;
-        const int32_t p = live && i > 0 ? block_of(t[i - 1]) : -1;
+        const int32_t e = block_of(tv[u]);
+        int32_t p = __shfl_up(e, 1);
+        if (lane == 0) p = before;
+        before = __shfl(e, 63);
         const bool wide = live && e - p > 32;
         if (live && !wide)
             for (int32_t q = p + 1; q <= e; ++q) seg[q] = (int32_t)i;
         for (uint64_t m = __ballot(wide); m; m &= m - 1) {
             const int l = __ffsll((unsigned long long)m) - 1;
             const int32_t q0 = __shfl(p, l) + 1, q1 = __shfl(e, l);
-            const int32_t v = (int32_t)(r + (tid & ~63) + l);
+            const int32_t v = (int32_t)(r + l);
             if (q1 - q0 < kSegWide) {
                 for (int32_t q = q0 + lane; q <= q1; q += 64) seg[q] = v;
             } else if (lane == 0) {
@@ -234,8 +248,9 @@ k_reg_seg(const RegTask* __restrict__ tasks, const int64_t* __restrict__ blk0, i
 // kRegTile apart) by C adjacent cells; its cells are gathered from the samples
 // straight into LDS (value sums in x, sample counts in y; the standardized
 // value is formed here), transformed along the rows and written with the pass
-// twiddles. Bound by the grid write: the grid is not written by a fill and
-// read back. 512 threads of 8 elements: the sample loads of one workgroup
+// twiddles: the grid is not written by a fill and read back. Bound by the chain
+// of each workgroup, gather, stages and write, with two on a CU: 2.9 TB/s, where a
+// copy reaches 4.9. 512 threads of 8 elements: the sample loads of one workgroup
 // overlap the transform of the other (two fit a CU's LDS). The batch above:
 // fill and first passes 2.1 ms, this 1.26 ms.
 constexpr int kFirstLgT = 12;
@@ -295,7 +310,8 @@ k_reg_first(fftk::PassArgs a, const RegTask* __restrict__ tasks, const IoBlock* 
                     if (i > i0 && reg_lat(tp[u], t_ref, inv_dt) == m) continue;  // not first
                     double sv = ok ? (xv[u] - mean) * inv_sd : 0.0, sn = 1.0;
                     // the other samples of the cell, in order
-                    for (int j = i + 1; j < i1;) {
+                    const bool run = i + 1 < i1 && reg_lat(t[i + 1], t_ref, inv_dt) == m;
+                    for (int j = run ? i + 1 : i1; j < i1;) {
                         double tj[kRunLoads], xj[kRunLoads];
 #pragma unroll
                         for (int q = 0; q < kRunLoads; ++q) {
