@@ -116,7 +116,11 @@ typedef enum { NCF_MIXED = 0, NCF_FP64 = 1 } ncf_precision_t;
  *   kernel's Fourier transform (diagnostic: its truncation error decays only
  *   as 1/f).
  * NCF_DIRECT: numerator and pair counts by the window scan (real-space
- *   estimator, Appendix B); with NCF_FP64 this is the plain FP64 GPU path. */
+ *   estimator, Appendix B); with NCF_FP64 this is the plain FP64 GPU path.
+ * The window scan adds a lag's terms by groups of outer samples that are
+ * sized by the call and by the workspace it may use, so its Gaussian and
+ * weighted sums of one series alone, in a batch, and by ncf_ccf_noalloc agree
+ * to rounding (1e-12), not bit for bit; a repeated call gives the same bits. */
 typedef enum { NCF_AUTO = 0, NCF_SPECTRAL = 1, NCF_DIRECT = 2 } ncf_method_t;
 
 #define NCF_DEVICE_POINTERS 0x1u

@@ -2253,7 +2253,11 @@ int CallRun::plan_spectral() {
 // tiles or more. Separate and fused call times, 20,000 daily samples each, h = 0.5:
 // 4 series (128 tiles) 132, 136 us; 16 (512 tiles) 173, 167 us; 128 (4096
 // tiles) 386, 361 us; at 0.9 samples per cell (300 series of 60,000) 1271,
-// 952 us. Below the line the grid stays in cache and the index pass costs more
+// 952 us. More samples per cell bear it out further (16 series of 20,000 days;
+// separate, fused): 16 per day 1.05 ms, 0.32; 48 per day 8.6, 0.74; 200 per day
+// 106, 3.1; in FP64 16 per day 2.6, 0.40; 200 per day 424, 4.4): the separate
+// spread's staged samples then reach the cells of a few threads, and the others
+// wait. Below the line the grid stays in cache and the index pass costs more
 // than the sweep it saves. The CCF ties (100 replicates of 20,000 + 20,000
 // samples: 884, 893 us): two grids of two series each would spread every
 // sample twice. Sizes of fewer tiles share one spread launch (FP64, 18 series on
