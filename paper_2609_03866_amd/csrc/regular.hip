@@ -833,12 +833,16 @@ int launch_reg_mid(const RegTask* d_tasks, const int64_t* d_pair0, int ntasks, i
     return NCF_OK;
 }
 
+constexpr int64_t kRegLagsWide = 256;
+
 int launch_reg_lags(const RegTask* d_tasks, const int64_t* d_lag0, int ntasks, int64_t nblocks,
                     hipStream_t st, double bytes) {
     if (ntasks <= 0 || nblocks <= 0) return NCF_OK;
     ProfScope p(st, "reg_lags", bytes, "bytes");
-    // 16 waves while the launch leaves CUs free
-    if (nblocks <= 512)
+    // 16 waves while the launch has a CU for each workgroup. 4 and 16 waves, 366 lags:
+    // one series of 1e6 samples (6 workgroups) 16.2, 11.6 us; 30 of 500,000 (180) 12.4,
+    // 12.3; 42 of 256,000 (252) 10.2, 10.7; 85 of 20,000 (510) 7.5, 10.4.
+    if (nblocks <= kRegLagsWide)
         hipLaunchKernelGGL(k_reg_lags<16>, dim3((unsigned)nblocks), dim3(1024), 0, st, d_tasks,
                            d_lag0, ntasks);
     else

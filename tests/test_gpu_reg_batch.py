@@ -50,3 +50,37 @@ def test_one_sample_per_cell():
     np.testing.assert_array_equal(out[1][0].cpu().numpy(), n - lags)
     assert took["reg_seg"] <= 0.95 * took["moments"]
     assert first <= 1.4 * took["reg_mid"]
+
+
+# lag workgroups (6 per series) on either side of one per CU and of two per CU
+@pytest.mark.parametrize("few,many,n", [(42, 43, 3000), (84, 88, 20000)])
+def test_lag_workgroups(few, many, n):
+    import torch
+    print(f"case: lags of {few} and {many} lattice series", flush=True)
+    dev = torch.device("cuda:0")
+    lags = torch.arange(366.0, dtype=torch.float64, device=dev)
+    took = []
+    for nser in (few, many):
+        rng = synth.rng_for(nser)
+        t = np.tile(np.arange(float(n)), nser)
+        x = np.sin(t / 9.0) + 0.5 * rng.normal(size=t.size)
+        t, x = (torch.as_tensor(a, device=dev) for a in (t, x))
+        offs = n * np.arange(nser + 1)
+        best, before = 1e9, 0.0
+        ncf.profile_enable(True)
+        ncf.profile_filter("reg_lags")
+        try:
+            for _ in range(8):
+                out = ncf.acf_regular_batch(offs, t, x, lags, 1.0, "rectangle", 0.5)
+                total = ncf.profile_read()["reg_lags"]["total_ms"]
+                best, before = min(best, total - before), total
+        finally:
+            ncf.profile_enable(False)
+            ncf.profile_filter(None)
+        took.append(best)
+        for i in (0, nser - 1):
+            c, b = ncf.acf_regular(t[:n], x[i * n:(i + 1) * n], lags, 1.0, "rectangle", 0.5)[:2]
+            assert float((out[0][i] - c).abs().max()) <= 1e-12
+            assert bool((out[1][i] == b).all())
+    print(f"ratio {took[0] / took[1]:.2f}", flush=True)
+    assert took[0] <= 1.15 * took[1]
