@@ -2007,7 +2007,10 @@ void CallRun::plan_window(WinLaunch& W) {
     // Tasks of an eighth of the launch's lags (the lag-0 scales) stay longer.
     //   up to: 64, or as many as leave 16,384 (rectangle 4096) items in the launch,
     //   or 1024 to 8192 (512 to 1024) in the series, by its lags;
-    //   down to: 2048 (1024) items in the launch, but 16 samples, and one per run;
+    //   down to: 3072 items in the launch (50,000 dense samples, 2048 and 3072 items:
+    //   942, 894 us); rectangle 1024, and then to 1434 (bursts of 31,000 samples, 324
+    //   lags, 1024 and 1448 items: 388, 298 us; but 100,000 samples, 401 lags, 1330
+    //   items by their range and 1449: 118, 137); but 16 samples, and one per run;
     //   where that leaves less than kWinItemsFew: one per wave.
     // An item of less than 33 lags has as many runs of outer samples as they leave
     // lanes for: a length below their number leaves lanes idle (2338 samples in
@@ -2020,18 +2023,21 @@ void CallRun::plan_window(WinLaunch& W) {
     };
     int shortest = 16;
     const double tiles_all = out_lags / lags_tile;
+    auto light = [&](const WinTask& T) { return (double)T.K / T.n_kt < lags_tile / 8.0; };
     auto longest = [&](const WinTask& T) {
+        if (light(T)) return rect ? 512 : 256;
         const double lags = (double)T.K / T.n_kt;
-        if (lags < lags_tile / 8.0) return rect ? 512 : 256;
         const double own = (double)T.n_out * T.n_kt /
                            (rect ? std::max(512.0, 16.0 * lags) : std::max(1024.0, 128.0 * lags));
         return (int32_t)std::min((double)jmax,
                                  std::max({64.0, tiles_all / (rect ? 4096.0 : 16384.0), own}));
     };
-    int32_t top = (int32_t)std::min((double)jmax, std::ceil(tiles_all / (rect ? 1024.0 : 2048.0)));
+    int32_t top = (int32_t)std::min((double)jmax, std::ceil(tiles_all / (rect ? 1024.0 : 3072.0)));
     auto length = [&](const WinTask& T) {
         const int runs = runs_of(T);
-        int32_t j = std::min(std::min(T.J, longest(T)), std::max({top, runs, shortest}));
+        const int32_t most = std::max(runs, shortest);
+        int32_t j = std::min(T.J, longest(T));
+        if (j > std::max(top, most)) j = std::max(rect ? top * 5 / 7 : top, most);
         j = (j + 3) & ~3;
         const int m = (j + runs - 1) / runs;
         return m > 1 && j < 0.85 * m * runs ? (m - 1) * runs : j;
@@ -2080,17 +2086,19 @@ void CallRun::plan_window(WinLaunch& W) {
     const int64_t want = round_up((int64_t)(2.0 * need) + 64, 64);
     const int grow_t = std::max(256, (int)std::min<double>(cap_t, want));
     const int64_t jtop = round_up(jneed, 64);
-    // items of few lags (e.g. the lag-0 scale tasks) grow within that
+    // tasks of few of the launch's lags (the lag-0 scales) grow within that
     // footprint until they hold ~8192 windows: a workgroup's searches and
-    // staging cost the same for any size (while the launch keeps enough)
+    // staging cost the same for any size (while the launch keeps enough). The
+    // others keep the length above: doubled, 24 FP64 pairs of 16,000 samples in
+    // bursts take 17.2 ms, so 12.
     int64_t tiles = 0;
     for (int i = 0; i < ntask; ++i) {
         WinTask& T = W.wt[i];
         const int64_t kin = std::min<int64_t>(T.K, 64);
         auto own = [&](int64_t j) { return ceil_div(T.n_out, j) * T.n_kt; };
         int64_t Jt = T.J;
-        while (Jt * 2 <= jtop && est_of(i, Jt * 2) <= 0.5 * W.cap && Jt * 2 * kin <= 8192 &&
-               total - own(Jt) + own(Jt * 2) >= kWinItemsFew) {
+        while (light(T) && Jt * 2 <= jtop && est_of(i, Jt * 2) <= 0.5 * W.cap &&
+               Jt * 2 * kin <= 8192 && total - own(Jt) + own(Jt * 2) >= kWinItemsFew) {
             total -= own(Jt) - own(Jt * 2);
             Jt *= 2;
         }
